@@ -11,15 +11,19 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcf.so")
-SOURCES = ["cf_abi.hip", "k_trace.hip", "k_coarse.hip", "k_select.hip", "k_reduce.hip", "k_fine.hip", "k_mc.hip", "k_enum.hip", "k_bisect.hip"]
+SOURCES = ["cf_abi.hip", "k_trace.hip", "k_coarse.hip", "k_select.hip", "k_reduce.hip", "k_fine.hip", "k_fine_reg.hip", "k_mc.hip", "k_enum.hip", "k_bisect.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include")]
-# The fine kernel is one function by design: every helper is inlined so that the
-# simulation state stays in registers and LDS (a call would move it to scratch).
-# The gated instantiation exceeds the AMDGPU inliner's default basic-block limit.
-FILE_FLAGS = {"k_fine.hip": ["-mllvm", "-amdgpu-inline-max-bb=3000"]}
+# The simulation kernels are one function each by design: every helper is inlined so
+# that the simulation state stays in registers and LDS (a call would move it to scratch).
+# They exceed the AMDGPU inliner's default basic-block limit.  k_fine_reg's control flow
+# is wave-uniform almost everywhere: left as scalar branches instead of being
+# restructured for divergence it issues an eighth fewer instructions.
+INLINE_ALL = ["-mllvm", "-amdgpu-inline-max-bb=3000"]
+FILE_FLAGS = {"k_fine.hip": INLINE_ALL,
+              "k_fine_reg.hip": INLINE_ALL + ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]}
 
 
 def build(verbose=False, jobs=8):

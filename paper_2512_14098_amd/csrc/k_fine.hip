@@ -36,7 +36,8 @@
 // Two instantiations of the kernel: k_fine<false> simulates thinker steps
 // one at a time and wakes the talker executors after every remote thinker
 // step; it serves models without a gated stage, where none of that is
-// reached.  k_fine<true>, used for models with a gated stage, also runs
+// reached, whose plans have more than 64 stage instances (k_fine_reg.hip
+// takes the others).  k_fine<true>, used for models with a gated stage, also runs
 // thinker stages in decode runs and replaces the per-step wake-ups by exact
 // wake times: a talker request becomes eligible at the visibility time of
 // the thinker token it waits for, the only state change not caused by an
@@ -54,23 +55,17 @@
 
 #include <mutex>
 
-#include "cf_internal.h"
+#include "cf_fine.h"
 #include "cf_run.h"
 
 namespace cf {
 namespace {
+using namespace fine;
 
-constexpr int kMaxSI = CF_MAX_EXEC * CF_MAX_COMP;  // stage instances
-static_assert(kMaxSI <= 512, "an LLM stage instance index fits the 9 bits of a gate word");
-constexpr int kChunk = 64;                          // queue chunk entries
 constexpr int kHist = 64;                           // k_fine<false>: ring of the last thinker step ends
 constexpr int kRing = 256;                          // k_fine<true>: thinker step-time ring
 constexpr int kKeep = 64;                           // k_fine<true>: completed steps kept in the ring
 constexpr uint32_t kThRun = kRing - kKeep;          // k_fine<true>: longest thinker decode run
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-
-enum { IT_BATCH = 0, IT_PREFILL = 1, IT_DECODE = 2, IT_FINISH = 3 };
-enum { DL_DELIVER = 0, DL_TICK = 1 };
 constexpr uint32_t MISC_OUTS = 15u;     // outputs still to finish
 constexpr uint32_t MISC_TH_DONE = 16u;  // thinker finished
 constexpr uint32_t MARK = 0x80000000u;  // gated running slot: in the current decode step
@@ -102,11 +97,6 @@ struct __attribute__((aligned(32))) Tim {
   double tfirst, tlast, tmedia;
   uint32_t thjoin, pad;
 };
-// a delay-line entry: due time and what is delivered (one 16-byte block)
-struct __attribute__((aligned(16))) DlEnt {
-  double t;
-  uint32_t v, pad;
-};
 // a request's record, its length attributes (copied from the trace at its
 // arrival) and its times side by side: one 64-byte block holds them all
 struct __attribute__((aligned(64))) Req {
@@ -116,50 +106,6 @@ struct __attribute__((aligned(64))) Req {
   Tim t;
 };
 static_assert(sizeof(Req) == 64 && __builtin_offsetof(Req, t) == 32, "request block");
-
-struct Layout {
-  size_t req;
-  size_t run, hist, mem, dl, pool, pool_next, pool_free;
-  size_t bytes;
-  int run_cap, hist_slots, n_chunks;
-  uint32_t dl_mask;
-};
-
-struct FineArgs {
-  KModel m;
-  int P;
-  const uint8_t *n_nodes, *node_comp, *node_rep, *node_gpus, *n_alt, *alt_w, *alt_node;
-  const uint16_t *node_batch;
-  const uint8_t *node_rep2, *node_gpus2, *node_w;  // a node's second configuration (NULL: none)
-  const uint16_t *node_batch2;
-  const int32_t *plan_ids;
-  int n_plans;
-  const double *rates;
-  int K;
-  const uint64_t *ticks, *rkey0, *rkey1;
-  const uint8_t *type;
-  const uint16_t *patches, *prompt, *out;
-  const uint32_t *aud_in, *aud_out, *akey;
-  int S, n;
-  uint32_t *met, *cnt, *status;
-  uint64_t *events;
-  double *lat;
-  const int32_t *lat_triples;
-  int n_lat;
-  uint32_t *hist;      // optional [n_plans][K][S][T][nb + 1] latency histograms
-  const double *tg;    // their target table [T][nb][4]
-  int nb;
-  char *slab;
-  Layout L;
-  unsigned int *ticket;
-  unsigned int total;
-  int nsi_cap;  // stage instances provided in LDS
-  int nl_cap, nt_cap;  // k_fine<true>: LLM stage instances and thinker ring slots provided in LDS
-  uint64_t lim_instants;  // instants a simulation may take (a test limit; ~0 = none)
-  // order in which a seed's (plan, rate) pairs are taken: entry j is i * K + k
-  // (null: rate index first, then plan)
-  const uint32_t *order;
-};
 
 // model tables read with per-lane (divergent) indices
 struct ModelLds {
@@ -214,11 +160,6 @@ struct SiLds {
 constexpr size_t kSiBytes = 1 + 1 + 1 + 1 + 2 + 2 + 4 * 7;
 // k_fine<true>: bytes per stage instance, per LLM stage instance, per thinker slot
 constexpr size_t kSiBytesG = 4 * 4, kLlmBytesG = 4 * 4 + 2, kThBytesG = 8 + 4;
-// a queue end, chunk c (-1: none) and position p <= kChunk in it, as one word
-// (chunk indices stay below 2^25: at most 2^26 requests on 8 components)
-__device__ __forceinline__ uint32_t qend(int c, int p) { return ((uint32_t)(c + 1) << 7) | (uint32_t)p; }
-__device__ __forceinline__ int qend_chunk(uint32_t w) { return (int)(w >> 7) - 1; }
-__device__ __forceinline__ int qend_pos(uint32_t w) { return (int)(w & 127u); }
 static_assert(sizeof(WaveShared) % 8 == 0, "the dynamic LDS table after WaveShared holds 8-byte words");
 // a wavefront's static LDS: k_fine<false> also holds the executors' times and
 // decode-run step counters
@@ -258,88 +199,6 @@ __device__ __forceinline__ int si_beff(const SiLds &si, int s) {
   else return si.beff[s];
 }
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x; }
-__device__ __forceinline__ uint32_t ru(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int ri(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint64_t ru64(uint64_t v) {
-  return ((uint64_t)ru((uint32_t)(v >> 32)) << 32) | ru((uint32_t)v);
-}
-__device__ __forceinline__ double rdb(double v) {
-  return __longlong_as_double((long long)ru64((uint64_t)__double_as_longlong(v)));
-}
-// the value lane x holds (x wave-uniform)
-__device__ __forceinline__ double lane_val(double v, int x) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, x);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), x);
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-__device__ __forceinline__ uint32_t lanes_below(uint64_t bal) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-}
-// wavefront minimum of a u32 through DPP row shifts and row broadcasts
-// (identity ~0 for lanes whose source is out of range); result in lane 63
-__device__ __forceinline__ uint32_t dpp_min_u32(uint32_t v) {
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x112, 0xf, 0xf, false));  // row_shr:2
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x113, 0xf, 0xf, false));  // row_shr:3
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x114, 0xf, 0xe, false));  // row_shr:4
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x118, 0xf, 0xc, false));  // row_shr:8
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)~0u, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-// minimum of non-negative doubles (or +inf) over the wavefront: the bit
-// patterns of such doubles order like the values, so the high words are
-// reduced first and the low words among the lanes holding that high word
-__device__ __forceinline__ double wave_min_time(double t) {
-  const uint64_t b = (uint64_t)__double_as_longlong(t);
-  const uint32_t hi = dpp_min_u32((uint32_t)(b >> 32));
-  const uint32_t lo = dpp_min_u32((uint32_t)(b >> 32) == hi ? (uint32_t)b : ~0u);
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-// inclusive prefix sum over the lanes through DPP: row_shr 1, 2, 4, 8 scan
-// each row of 16 lanes (identity 0 where the source is out of range), then
-// row_bcast 15 and row_bcast 31 carry the row totals into the later rows.
-// Needs every lane active.
-__device__ __forceinline__ uint32_t dpp_scan_add(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return v;
-}
-// wavefront sum (uniform result)
-__device__ __forceinline__ uint32_t dpp_sum_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)dpp_scan_add(v), 63);
-}
-// exclusive prefix sum of v over the lanes, and the total
-__device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t &total) {
-  const uint32_t x = dpp_scan_add(v);
-  total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-  return x - v;
-}
-
-// Device memory (global address space) addressed by a 32-bit byte offset
-// from a base held in scalar registers: loads and stores take the
-// scalar-base + vector-offset form, with no 64-bit address arithmetic per
-// lane.  Every array the kernel indexes is far below 4 GiB.
-#define CF_GLOBAL __attribute__((address_space(1)))
-template <typename T>
-struct GPtr {
-  CF_GLOBAL T *p;
-  __device__ __forceinline__ CF_GLOBAL T &operator[](uint32_t i) const {
-    return *(CF_GLOBAL T *)((CF_GLOBAL char *)p + i * (uint32_t)sizeof(T));
-  }
-  __device__ __forceinline__ GPtr operator+(uint32_t i) const { return GPtr{&(*this)[i]}; }
-};
-template <typename T>
-__device__ __forceinline__ GPtr<T> gptr_at(char *base, size_t off) {
-  return GPtr<T>{(CF_GLOBAL T *)(base + off)};
-}
 // One word of the running slots, which lie interleaved in the slab
 // (k_fine<true>: request, key, gate word, join step; k_fine<false>: request,
 // key): slot i's word is 4 << sh bytes after slot i - 1's, so a slot's words
@@ -353,7 +212,6 @@ struct SlotPtr {
   __device__ __forceinline__ SlotPtr operator+(uint32_t i) const { return SlotPtr{&(*this)[i], sh}; }
 };
 // k_fine<true>: the four words of a running slot, read in one 16-byte load
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Slot4 {
   uint32_t r, k, g, q;
 };
@@ -365,12 +223,6 @@ __device__ __forceinline__ void slot_put(const SlotPtr &rr, uint32_t j, const Sl
   const u32x4 v = {w.r, w.k, w.g, w.q};
   *(CF_GLOBAL u32x4 *)((CF_GLOBAL char *)rr.p + (j << 4)) = v;
 }
-// element o of a read-only input array
-template <typename T>
-__device__ __forceinline__ T gload(const T *p, size_t o) {
-  return *(const CF_GLOBAL T *)((const CF_GLOBAL char *)p + (uint32_t)o * (uint32_t)sizeof(T));
-}
-
 struct Sim {
   const FineArgs *A;
   WaveShared *sh;
@@ -2482,6 +2334,10 @@ cf_status eval_fine(const cf_model_desc *model, const cf_plan_table *plans, cons
   hipLaunchKernelGGL(k_fine_reset, dim3(1), dim3(1), 0, s, a.ticket);
   if (a.m.gated_mask)
     hipLaunchKernelGGL(k_fine<true>, dim3((unsigned)waves), dim3(64), lds, s, (const FineArgs *)args_dev);
+  // one lane per stage instance, 32-bit offsets in a wavefront's memory: the
+  // simulator in registers takes a third less time than the one in LDS
+  else if (caps[0] <= (unsigned)kRegStages && a.L.bytes < (1ull << 32))
+    launch_fine_reg((const FineArgs *)args_dev, (unsigned)waves, s);
   else
     hipLaunchKernelGGL(k_fine<false>, dim3((unsigned)waves), dim3(64), lds, s, (const FineArgs *)args_dev);
   st = hip_check(hipGetLastError(), "cf_eval_fine launch");
