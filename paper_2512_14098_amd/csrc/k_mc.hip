@@ -466,98 +466,124 @@ __global__ void __launch_bounds__(64) k_mc(KModel m, McView V) {
 // many rows, so a dominated row is dominated by some row that nothing
 // dominates, and such a row is never pruned.  Two passes use this:
 //   1. each block of kParBlock consecutive rows prunes the rows another row
-//      of the same block dominates and lists its survivors;
-//   2. each survivor is tested against the survivors of every block (which
-//      include every undominated row), a block stopping once all of its
-//      survivors are dominated.
+//      of the same block dominates and appends its survivors to a dense list;
+//   2. each survivor is tested against every survivor (which include every
+//      undominated row).
 // The result is the plain all-pairs definition; the work is n * kParBlock
-// plus (survivors)^2 comparisons instead of n^2.
+// plus (survivors)^2 comparisons instead of n^2.  The second pass is bound by
+// vector issue (about 3 T + 4 instructions per pair of rows).  16,000 rows of
+// four types fill only 63 blocks of 256 rows, so its grid also splits the
+// survivors compared against over kParSlices blocks; with the row length a
+// template argument a row is T registers and the inner loop reads the other
+// row by broadcast LDS loads that are issued together.  A row is marked by any
+// slice that finds a dominating row (they all write the same bytes).
+// 16,000 rows of four types, the second pass: 3.27 ms before, 0.10 ms now (the first 0.085, 0.028).
 constexpr int kParBlock = 256;
+constexpr int kParSlices = 32;
+constexpr int kParUnroll = 4;
 
-__device__ __forceinline__ bool dominates(const double *a, const double *b, int T) {
-  bool ge = true, gt = false;
+// whether some row k0..k0+kParUnroll-1 of tile dominates mine
+template <int T>
+__device__ __forceinline__ bool any_dominates(const double *tile, int k0, int cnt, const double *mine, int self) {
+  bool any = false;
 #pragma unroll
-  for (int t = 0; t < CF_MAX_TYPES; t++) {
-    if (t < T) {
-      ge = ge && !(a[t] < b[t]);
-      gt = gt || a[t] > b[t];
+  for (int q = 0; q < kParUnroll; q++) {
+    const int k = k0 + q;
+    bool ge = true, gt = false;
+#pragma unroll
+    for (int t = 0; t < T; t++) {
+      const double o = tile[k * T + t];
+      ge = ge && !(o < mine[t]);
+      gt = gt || o > mine[t];
     }
+    any = any || (ge && gt && k < cnt && k != self);
   }
-  return ge && gt;
+  return any;
 }
 
-__device__ __forceinline__ void prune(int i, uint8_t *keep, const int32_t *plan_ids, uint8_t *flags, int n_flags,
-                                      bool dominated) {
-  keep[i] = dominated ? 0 : 1;
-  if (flags && dominated) {
+__device__ __forceinline__ void prune(int i, uint8_t *keep, const int32_t *plan_ids, uint8_t *flags, int n_flags) {
+  keep[i] = 0;
+  if (flags) {
     const int p = plan_ids[i];
     if (p >= 0 && p < n_flags) flags[p] = (uint8_t)(flags[p] & ~CF_FLAG_KEEP);
   }
 }
 
-__global__ void __launch_bounds__(kParBlock) k_pareto_local(const double *g, int n, int T, uint8_t *keep,
+// surv[0]: number of survivors, their rows from surv + 1 on
+__global__ void k_pareto_init(int32_t *surv) { surv[0] = 0; }
+
+template <int T>
+__global__ void __launch_bounds__(kParBlock) k_pareto_local(const double *g, int n, uint8_t *keep,
                                                             const int32_t *plan_ids, uint8_t *flags, int n_flags,
-                                                            int32_t *surv, int32_t *surv_n) {
-  __shared__ double tile[kParBlock * CF_MAX_TYPES];
-  __shared__ int cnt_s;
-  const int i0 = blockIdx.x * kParBlock, i = i0 + threadIdx.x;
+                                                            int32_t *surv) {
+  __shared__ double tile[(kParBlock + kParUnroll) * T];
+  __shared__ int cnt_s, base_s;
+  const int tid = threadIdx.x, i0 = blockIdx.x * kParBlock, i = i0 + tid;
   const int cnt = n - i0 < kParBlock ? n - i0 : kParBlock;
-  if (threadIdx.x == 0) cnt_s = 0;
-  for (int q = threadIdx.x; q < cnt * T; q += kParBlock) tile[q] = g[(size_t)i0 * T + q];
+  if (tid == 0) cnt_s = 0;
+  for (int q = tid; q < (kParBlock + kParUnroll) * T; q += kParBlock) tile[q] = q < cnt * T ? g[(size_t)i0 * T + q] : 0.0;
   __syncthreads();
-  if (i < n) {
-    double mine[CF_MAX_TYPES];
+  bool kept = i < n;
+  if (kept) {
+    double mine[T];
 #pragma unroll
-    for (int t = 0; t < CF_MAX_TYPES; t++) mine[t] = t < T ? tile[threadIdx.x * T + t] : 0.0;
-    bool dominated = false;
-    for (int jj = 0; jj < cnt && !dominated; jj++) {
-      double other[CF_MAX_TYPES];
-#pragma unroll
-      for (int t = 0; t < CF_MAX_TYPES; t++) other[t] = t < T ? tile[jj * T + t] : 0.0;
-      dominated = jj != (int)threadIdx.x && dominates(other, mine, T);
-    }
-    if (dominated)
-      prune(i, keep, plan_ids, flags, n_flags, true);
-    else
-      surv[i0 + atomicAdd(&cnt_s, 1)] = i;
+    for (int t = 0; t < T; t++) mine[t] = tile[tid * T + t];
+    for (int k = 0; k < cnt && kept; k += kParUnroll) kept = !any_dominates<T>(tile, k, cnt, mine, tid);
+    if (kept) keep[i] = 1;
+    else prune(i, keep, plan_ids, flags, n_flags);
   }
+  int pos = 0;
+  if (kept) pos = atomicAdd(&cnt_s, 1);
   __syncthreads();
-  if (threadIdx.x == 0) surv_n[blockIdx.x] = cnt_s;
+  if (tid == 0) base_s = atomicAdd(surv, cnt_s);
+  __syncthreads();
+  if (kept) surv[1 + base_s + pos] = i;
 }
 
-__global__ void __launch_bounds__(kParBlock) k_pareto_global(const double *g, int n, int T, uint8_t *keep,
-                                                             const int32_t *plan_ids, uint8_t *flags, int n_flags,
-                                                             const int32_t *surv, const int32_t *surv_n) {
-  __shared__ double tile[kParBlock * CF_MAX_TYPES];
-  const int nb = (n + kParBlock - 1) / kParBlock;
-  const int b = blockIdx.x, ns = surv_n[b];
-  const int i = (int)threadIdx.x < ns ? surv[b * kParBlock + threadIdx.x] : -1;
-  double mine[CF_MAX_TYPES];
+template <int T>
+__global__ void __launch_bounds__(kParBlock) k_pareto_global(const double *g, uint8_t *keep, const int32_t *plan_ids,
+                                                             uint8_t *flags, int n_flags, const int32_t *surv) {
+  __shared__ double tile[(kParBlock + kParUnroll) * T];
+  const int tid = threadIdx.x, ns = surv[0], j = blockIdx.x * kParBlock + tid;
+  if ((int)blockIdx.x * kParBlock >= ns) return;
+  const int i = j < ns ? surv[1 + j] : -1;
+  double mine[T];
 #pragma unroll
-  for (int t = 0; t < CF_MAX_TYPES; t++) mine[t] = (i >= 0 && t < T) ? g[(size_t)i * T + t] : 0.0;
-  bool dominated = false;
-  for (int b2 = 0; b2 < nb; b2++) {
-    const int n2 = surv_n[b2];
-    for (int q = threadIdx.x; q < n2 * T; q += kParBlock) {
-      const int k = q / T, t = q - k * T;
-      tile[q] = g[(size_t)surv[b2 * kParBlock + k] * T + t];
+  for (int t = 0; t < T; t++) mine[t] = i >= 0 ? g[(size_t)i * T + t] : 0.0;
+  bool dominated = i < 0;  // lanes without a row have nothing to find
+  const int nt = (ns + kParBlock - 1) / kParBlock;
+  for (int b = blockIdx.y; b < nt; b += gridDim.y) {
+    const int k0 = b * kParBlock, cnt = ns - k0 < kParBlock ? ns - k0 : kParBlock;
+    {
+      const int row = tid < cnt ? surv[1 + k0 + tid] : -1;
+#pragma unroll
+      for (int t = 0; t < T; t++) tile[tid * T + t] = row >= 0 ? g[(size_t)row * T + t] : 0.0;
+      if (tid < kParUnroll * T) tile[kParBlock * T + tid] = 0.0;
     }
     __syncthreads();
-    if (i >= 0 && !dominated) {
-      for (int k = 0; k < n2; k++) {
-        double other[CF_MAX_TYPES];
-#pragma unroll
-        for (int t = 0; t < CF_MAX_TYPES; t++) other[t] = t < T ? tile[k * T + t] : 0.0;
-        if (dominates(other, mine, T)) {
-          dominated = true;
-          break;
-        }
+    // a row never dominates itself, so the own row needs no exception
+    for (int k = 0; k < cnt && !dominated; k += kParUnroll) {
+      if (any_dominates<T>(tile, k, cnt, mine, -1)) {
+        dominated = true;
+        prune(i, keep, plan_ids, flags, n_flags);
       }
     }
     // also the barrier before the next tile overwrites this one
-    if (!__syncthreads_or(i >= 0 && !dominated)) break;
+    if (!__syncthreads_or(!dominated)) break;
   }
-  if (i >= 0) prune(i, keep, plan_ids, flags, n_flags, dominated);
+}
+
+template <int T>
+void launch_pareto(const double *g, int n, uint8_t *keep, const int32_t *plan_ids, uint8_t *flags, int n_flags,
+                   int32_t *surv, hipStream_t s) {
+  const unsigned nb = (unsigned)((n + kParBlock - 1) / kParBlock);
+  hipLaunchKernelGGL(k_pareto_init, dim3(1), dim3(1), 0, s, surv);
+  hipLaunchKernelGGL(k_pareto_local<T>, dim3(nb), dim3(kParBlock), 0, s, g, n, keep, plan_ids, flags, n_flags, surv);
+  // more slices than tiles would find nothing to do; one block needs none
+  const unsigned slices = nb < (unsigned)kParSlices ? nb : (unsigned)kParSlices;
+  if (nb > 1)
+    hipLaunchKernelGGL(k_pareto_global<T>, dim3(nb, slices), dim3(kParBlock), 0, s, g, keep, plan_ids, flags, n_flags,
+                       surv);
 }
 
 }  // namespace
@@ -675,16 +701,19 @@ extern "C" cf_status cf_pareto(const double *goodput_t_dev, int32_t n, int32_t T
   if (flags_dev && n_flags < 0) return set_error(CF_EINVAL, "n_flags");
   if (n == 0) return CF_OK;
   if (!goodput_t_dev || !keep_dev) return set_error(CF_EINVAL, "NULL device array");
-  const int nb = (n + kParBlock - 1) / kParBlock;
   cf_status st = CF_OK;
-  int32_t *surv = (int32_t *)scratch_get(SCR_PARETO, sizeof(int32_t) * ((size_t)nb * kParBlock + nb), &st);
+  int32_t *surv = (int32_t *)scratch_get(SCR_PARETO, sizeof(int32_t) * ((size_t)n + 1), &st);
   if (!surv) return st;
-  int32_t *surv_n = surv + (size_t)nb * kParBlock;
-  hipLaunchKernelGGL(k_pareto_local, dim3((unsigned)nb), dim3(kParBlock), 0, as_stream(stream), goodput_t_dev, n, T,
-                     keep_dev, plan_ids_dev, flags_dev, n_flags, surv, surv_n);
-  st = hip_check(hipGetLastError(), "cf_pareto launch");
-  if (st != CF_OK) return st;
-  hipLaunchKernelGGL(k_pareto_global, dim3((unsigned)nb), dim3(kParBlock), 0, as_stream(stream), goodput_t_dev, n, T,
-                     keep_dev, plan_ids_dev, flags_dev, n_flags, surv, surv_n);
+  hipStream_t s = as_stream(stream);
+  switch (T) {
+    case 1: launch_pareto<1>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    case 2: launch_pareto<2>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    case 3: launch_pareto<3>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    case 4: launch_pareto<4>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    case 5: launch_pareto<5>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    case 6: launch_pareto<6>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    case 7: launch_pareto<7>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+    default: launch_pareto<8>(goodput_t_dev, n, keep_dev, plan_ids_dev, flags_dev, n_flags, surv, s); break;
+  }
   return hip_check(hipGetLastError(), "cf_pareto launch");
 }
