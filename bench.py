@@ -31,6 +31,7 @@ METRIC = "simulated request-events/sec and candidate plans fully evaluated/sec, 
 PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9 / 1e12  # T lane-ops/s: CUs x SIMDs x lanes x clock
 OPS_PER_EVENT = 4.0  # algorithmic lane-ops per request-event
 KERNEL_SOURCES = ("paper_2512_14098_amd/csrc/k_fine.hip", "paper_2512_14098_amd/csrc/k_fine_reg.hip",
+                  "paper_2512_14098_amd/csrc/k_fine_gate.hip", "paper_2512_14098_amd/csrc/cf_fine_reg.h",
                   "paper_2512_14098_amd/csrc/cf_fine.h", "paper_2512_14098_amd/csrc/cf_internal.h",
                   "paper_2512_14098_amd/csrc/cf_run.h")
 MC_KERNEL_SOURCES = ("paper_2512_14098_amd/csrc/k_mc.hip", "paper_2512_14098_amd/csrc/cf_internal.h",

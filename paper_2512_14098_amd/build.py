@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcf.so")
-SOURCES = ["cf_abi.hip", "k_trace.hip", "k_coarse.hip", "k_select.hip", "k_reduce.hip", "k_fine.hip", "k_fine_reg.hip", "k_mc.hip", "k_enum.hip", "k_bisect.hip"]
+SOURCES = ["cf_abi.hip", "k_trace.hip", "k_coarse.hip", "k_select.hip", "k_reduce.hip", "k_fine.hip", "k_fine_reg.hip", "k_fine_gate.hip", "k_mc.hip", "k_enum.hip", "k_bisect.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -23,7 +23,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 # restructured for divergence it issues an eighth fewer instructions.
 INLINE_ALL = ["-mllvm", "-amdgpu-inline-max-bb=3000"]
 FILE_FLAGS = {"k_fine.hip": INLINE_ALL,
-              "k_fine_reg.hip": INLINE_ALL + ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]}
+              "k_fine_reg.hip": INLINE_ALL + ["-mllvm", "-structurizecfg-skip-uniform-regions=true"],
+              "k_fine_gate.hip": INLINE_ALL + ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]}
 
 
 def build(verbose=False, jobs=8):

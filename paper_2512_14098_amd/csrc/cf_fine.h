@@ -168,5 +168,10 @@ __device__ __forceinline__ T gload(const T *p, size_t o) {
 constexpr int kRegStages = 64;
 void launch_fine_reg(const FineArgs *args, unsigned waves, hipStream_t s);
 
+// k_fine_gate.hip: the same for models whose only LLM components are one gate
+// source and the one component gated by it.
+bool fine_gate_takes(const KModel &m);
+void launch_fine_gate(const FineArgs *args, int n_comp, unsigned waves, hipStream_t s);
+
 }  // namespace fine
 }  // namespace cf

@@ -89,4 +89,17 @@ constexpr double run_walk(double e, double d, uint32_t n, double stop, uint32_t 
   return e;
 }
 
+// Step of a duration d > 0 inside the binade of biased exponent ex, in units of
+// the binade's spacing, where it is the same from every point of the binade's
+// grid: d lies in a lower binade and d/u is no odd multiple of 1/2.  0 if it
+// is not (or d/u rounds to 0).
+constexpr uint64_t step_units(double d, int ex) {
+  constexpr uint64_t kMant = (1ull << 52) - 1;
+  const uint64_t bd = __builtin_bit_cast(uint64_t, d);
+  const int s = ex - (int)(bd >> 52);
+  if ((bd >> 52) == 0 || s <= 0 || s > 53) return 0;
+  const uint64_t md = (bd & kMant) | (1ull << 52), half = 1ull << (s - 1);
+  return (md & ((half << 1) - 1)) == half ? 0 : (md + half) >> s;
+}
+
 }  // namespace cf

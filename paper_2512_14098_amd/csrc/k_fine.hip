@@ -2332,7 +2332,11 @@ cf_status eval_fine(const cf_model_desc *model, const cf_plan_table *plans, cons
     if (st != CF_OK) return st;
   }
   hipLaunchKernelGGL(k_fine_reset, dim3(1), dim3(1), 0, s, a.ticket);
-  if (a.m.gated_mask)
+  // one thinker and one talker: executors in lanes, a tenth to a quarter faster
+  // than the stage table in LDS (32-bit offsets in a wavefront's memory)
+  if (fine_gate_takes(a.m) && a.L.bytes < (1ull << 32))
+    launch_fine_gate((const FineArgs *)args_dev, a.m.nc, (unsigned)waves, s);
+  else if (a.m.gated_mask)
     hipLaunchKernelGGL(k_fine<true>, dim3((unsigned)waves), dim3(64), lds, s, (const FineArgs *)args_dev);
   // one lane per stage instance, 32-bit offsets in a wavefront's memory: the
   // simulator in registers takes a third less time than the one in LDS
