@@ -4,15 +4,16 @@
 // Logical plans are few (hundreds to thousands) and are built on the host.
 // Physical plans are many (a logical plan of five nodes on 64 GPUs has
 // billions), so they are numbered and produced on the device by unranking:
-//   - per logical plan, a table cnt[v][b] = number of executor assignments
-//     of nodes v.. within b GPUs (one block per logical plan, the budgets
-//     across threads, the nodes from the last to the first);
+//   - per logical plan, cnt[v][b] = number of executor assignments of nodes
+//     v.. within b GPUs (one block per logical plan, the budgets across
+//     threads, the nodes from the last to the first), kept as its running
+//     sums over b (cum_row), or itself where nodes hold two configurations;
 //   - offsets = exclusive prefix sum of cnt[0][N] * 9^(types with two
 //     alternatives);
 //   - four consecutive plan indices per thread: for each, the logical plan by
-//     binary search in the offsets, the routing weights as base-9 digits of
-//     the index within it, the executor assignment by walking the table (at
-//     node v with budget b, the candidates (k, n) in order each own
+//     counting the offsets once per block, the routing weights as base-9
+//     digits of the index within it, the executor assignment by walking the
+//     table (at node v with budget b, the candidates (k, n) in order each own
 //     cnt[v+1][b - gpus_k n] consecutive numbers); the plan-table columns
 //     are written slot-major, four plans per 32-bit store, so a wavefront
 //     fills 256 consecutive bytes of a slot row per store instruction.
@@ -92,9 +93,24 @@ struct EnumView {
   int N;
   const cf_logical *logical;
   int n_logical;
-  uint64_t *tab;      // [n_logical][kTabSize]
+  int ng;             // most GPU options of a component
+  uint64_t *tab;      // [n_logical][tab_size]: cum_row rows, or cnt[v][b] with second configurations
   uint64_t *totals;   // [n_logical]
 };
+
+// u64 entries of one logical plan's table
+__host__ __device__ __forceinline__ size_t tab_size(bool het, int ng) {
+  return het ? (size_t)kTabSize : (size_t)CF_MAX_NODES * ng * kTabStride;
+}
+
+// Node v, GPU option gi of plan l's table: row[b] = the assignments of nodes v.. within b GPUs
+// whose node v takes option gi and one given batch size, the sum of cnt[v+1][b - g n] over
+// n >= 1.  row[b] - row[b - g n] of them have at most n executors at v, so a rank's batch size
+// follows from whole rows and its n from a binary search, instead of one table read per
+// (batch size, n) passed over.
+__device__ __forceinline__ const uint64_t *cum_row(const EnumView &V, int l, int v, int gi) {
+  return V.tab + (size_t)l * tab_size(false, V.ng) + (size_t)((v * V.ng + gi) * kTabStride);
+}
 
 __device__ __forceinline__ uint64_t sat_add(uint64_t a, uint64_t b) { return a > ~0ull - b ? ~0ull : a + b; }
 __device__ __forceinline__ uint64_t sat_mul(uint64_t a, uint64_t b) { return (b && a > ~0ull / b) ? ~0ull : a * b; }
@@ -123,6 +139,7 @@ __global__ void __launch_bounds__(128) k_enum_table(cf_enum_opts o, EnumView V) 
   stage_opts(so, o, threadIdx.x, blockDim.x);
   const cf_logical &L = V.logical[l];
   const int nv = L.n_nodes <= CF_MAX_NODES ? L.n_nodes : CF_MAX_NODES;
+  uint64_t *out = V.tab + (size_t)l * tab_size(o.het, V.ng);
   if (b <= V.N) cnt[nv][b] = 1;
   __syncthreads();
   for (int v = nv - 1; v >= 0; v--) {
@@ -133,6 +150,7 @@ __global__ void __launch_bounds__(128) k_enum_table(cf_enum_opts o, EnumView V) 
         const int g = so.gpu[c0][gi];
         uint64_t per_cfg = 0;
         for (int n = 1; g * n <= b; n++) per_cfg = sat_add(per_cfg, cnt[v + 1][b - g * n]);
+        if (!o.het) out[(v * V.ng + gi) * kTabStride + b] = per_cfg;
         for (int bi = 0; bi < so.n_batch[c0]; bi++) tot = sat_add(tot, per_cfg);
       }
       if (o.het) {
@@ -150,8 +168,8 @@ __global__ void __launch_bounds__(128) k_enum_table(cf_enum_opts o, EnumView V) 
     }
     __syncthreads();
   }
-  uint64_t *out = V.tab + (size_t)l * kTabSize;
-  for (int i = threadIdx.x; i < (nv + 1) * kTabStride; i += blockDim.x) out[i] = (&cnt[0][0])[i];
+  if (o.het)
+    for (int i = threadIdx.x; i < (nv + 1) * kTabStride; i += blockDim.x) out[i] = (&cnt[0][0])[i];
   if (threadIdx.x == 0) {
     uint64_t tot = cnt[0][V.N];
     for (int t = 0; t < CF_MAX_TYPES; t++)
@@ -205,10 +223,86 @@ struct Cursor {
   uint32_t w;   // routing weights, 4 bits per type with two alternatives, in type order
 };
 
-__device__ Cursor locate(const EnumView &V, const uint64_t *offsets, uint64_t idx, bool valid) {
+// What the consecutive plans of a block share.  Spaces hold many plans per logical plan, so a
+// block nearly always lies within one: its rank is divided by the routing digits once, a
+// thread's plan follows by 32-bit arithmetic, and the plan's record is read from LDS.
+struct BlockPos {
+  int lo, hi;        // logical plans of the block's first and last plan
+  uint32_t R, r0;    // 9^(types with two alternatives) of lo, and the first plan's routing rank
+  uint64_t q0;       // the first plan's executor-assignment rank
+  int na2;
+  alignas(8) uint8_t route[CF_MAX_TYPES][2][CF_MAX_COMP];  // lo's record
+  uint8_t comp[CF_MAX_NODES], n_alt[CF_MAX_TYPES];
+  uint8_t nv;
+};
+
+// Fills bp for the plans first..last (last < offsets[n_logical]); all threads of the block, ends
+// with a barrier.  offsets[l] never decreases: the plan's logical plan is the number of
+// offsets up to its index, less one, counted by all threads at once.
+__device__ __forceinline__ void block_pos(BlockPos &bp, const EnumView &V, const uint64_t *offsets, uint64_t first,
+                                          uint64_t last) {
+  const int tid = threadIdx.x;
+  if (tid == 0) bp.lo = bp.hi = -1;
+  __syncthreads();
+  int nlo = 0, nhi = 0;
+  for (int base = 0; base < V.n_logical; base += blockDim.x) {
+    const uint64_t x = base + tid < V.n_logical ? offsets[base + tid] : ~0ull;
+    nlo += __popcll(__ballot(base + tid < V.n_logical && x <= first));
+    nhi += __popcll(__ballot(base + tid < V.n_logical && x <= last));
+  }
+  if ((tid & 63) == 0) {
+    atomicAdd(&bp.lo, nlo);
+    atomicAdd(&bp.hi, nhi);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    if (bp.lo < 0) bp.lo = 0;
+    if (bp.hi < bp.lo) bp.hi = bp.lo;
+  }
+  __syncthreads();
+  const cf_logical &L = V.logical[bp.lo];
+  for (int i = tid; i < CF_MAX_TYPES * 2 * CF_MAX_COMP; i += blockDim.x)
+    (&bp.route[0][0][0])[i] = (&L.alt_node[0][0][0])[i];
+  if (tid < CF_MAX_NODES) bp.comp[tid] = L.node_comp[tid];
+  if (tid < CF_MAX_TYPES) bp.n_alt[tid] = L.n_alt[tid];
+  if (tid == 0) {
+    bp.nv = L.n_nodes;
+    int na2 = 0;
+    for (int t = 0; t < CF_MAX_TYPES; t++) na2 += L.n_alt[t] == 2;
+    uint32_t R = 1;
+    for (int i = 0; i < na2; i++) R *= 9;
+    const uint64_t local = first - offsets[bp.lo];
+    bp.na2 = na2;
+    bp.R = R;
+    bp.q0 = local / R;
+    bp.r0 = (uint32_t)(local - bp.q0 * R);
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void set_digits(Cursor &c, uint32_t r, int na2) {
+  c.w = 0;
+  for (int i = na2 - 1; i >= 0; i--) {  // lowest type is the most significant digit
+    c.w |= (r % 9 + 1) << (4 * i);
+    r /= 9;
+  }
+}
+
+// The cursor of the block's plan number d (index idx = first + d).
+__device__ Cursor locate(const EnumView &V, const uint64_t *offsets, const BlockPos &bp, uint64_t idx, uint32_t d,
+                         bool valid) {
   Cursor c;
+  c.b = V.N;
   c.ok = valid && idx < offsets[V.n_logical];
-  int lo = 0, hi = V.n_logical;  // offsets[lo] <= idx < offsets[hi]
+  c.l = bp.lo;
+  if (bp.lo == bp.hi) {  // one logical plan in the block
+    const uint32_t x = bp.r0 + d, dq = x / bp.R;  // below 9^8 + the block's plans
+    c.nv = c.ok ? bp.nv : 0;
+    c.q = bp.q0 + dq;
+    set_digits(c, x - dq * bp.R, bp.na2);
+    return c;
+  }
+  int lo = bp.lo, hi = bp.hi + 1;  // offsets[lo] <= idx < offsets[hi]
   if (c.ok) {
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -221,16 +315,10 @@ __device__ Cursor locate(const EnumView &V, const uint64_t *offsets, uint64_t id
   const uint64_t local = c.ok ? idx - offsets[lo] : 0;
   int na2 = 0;
   for (int t = 0; t < CF_MAX_TYPES; t++) na2 += L.n_alt[t] == 2;
-  uint64_t R = 1;
+  uint32_t R = 1;
   for (int i = 0; i < na2; i++) R *= 9;
-  uint64_t r = local % R;
   c.q = local / R;
-  c.w = 0;
-  for (int i = na2 - 1; i >= 0; i--) {  // lowest type is the most significant digit
-    c.w |= (uint32_t)(r % 9 + 1) << (4 * i);
-    r /= 9;
-  }
-  c.b = V.N;
+  set_digits(c, (uint32_t)(local - c.q * R), na2);
   return c;
 }
 
@@ -241,16 +329,61 @@ struct NodeCfg {
   uint16_t batch2;
 };
 
-// Node v of the plan at cursor c: the candidates (k, n) in order own
-// cnt[v+1][b - gpus_k n] consecutive ranks each; with het, then the
-// candidates (k1, k2, n1, n2, w) own cnt[v+1][b - gpus_k1 n1 - gpus_k2 n2]
-// each.
-__device__ NodeCfg place(const EnumView &V, const OptsLds &so, Cursor &c, int v, bool het) {
+// Node v (component set comp) of the plan at cursor c in a space of one configuration per node:
+// the candidates (GPU option gi, batch size bi, n) in order own cnt[v+1][b - gpus_gi n]
+// consecutive ranks each.  False: no candidate holds the rank.  step: the largest power of two
+// up to the GPU budget.
+__device__ __forceinline__ bool place_one(const EnumView &V, const OptsLds &so, Cursor &c, int v, int comp, int step,
+                                          int &c0, int &gi, int &bi, int &n) {
+  c0 = comp ? __ffs(comp) - 1 : 0;
+  const int nb = so.n_batch[c0];
+  for (gi = 0; gi < so.n_gpu[c0]; gi++) {
+    const uint64_t *row = cum_row(V, c.l, v, gi);
+    const uint64_t S = row[c.b];
+    bi = 0;
+    while (bi < nb && c.q >= S) {
+      c.q -= S;
+      bi++;
+    }
+    if (bi == nb) continue;
+    // most executors passed over: row[b - g t] >= S - q holds up to it and for no larger t
+    const int g = so.gpu[c0][gi];
+    const uint64_t left = S - c.q;
+    int t = 0;
+    uint64_t at = S;
+    for (int d = step; d; d >>= 1) {
+      const int bb = c.b - g * (t + d);
+      const uint64_t x = bb >= 0 ? row[bb] : 0ull;
+      if (x >= left) {
+        t += d;
+        at = x;
+      }
+    }
+    c.q -= S - at;
+    n = t + 1;
+    c.b -= g * n;
+    return true;
+  }
+  return false;
+}
+
+// Node v of the plan at cursor c; with het (a table of cnt) the candidates (k, n), then the
+// candidates (k1, k2, n1, n2, w), which own cnt[v+1][b - gpus_k1 n1 - gpus_k2 n2] each.
+__device__ NodeCfg place(const EnumView &V, const OptsLds &so, const BlockPos &bp, Cursor &c, int v, bool het,
+                         int step) {
   NodeCfg r = {0, 0, 0, 0, 0, 0, 10, 0};
   if (v >= c.nv) return r;
-  const cf_logical &L = V.logical[c.l];
+  r.comp = bp.lo == bp.hi ? bp.comp[v] : V.logical[c.l].node_comp[v];
+  if (!het) {
+    int k0, gi, bi, n;
+    if (place_one(V, so, c, v, r.comp, step, k0, gi, bi, n)) {
+      r.rep = (uint8_t)n;
+      r.gpus = so.gpu[k0][gi];
+      r.batch = so.batch[k0][bi];
+    }
+    return r;
+  }
   const uint64_t *tab = V.tab + (size_t)c.l * kTabSize + (size_t)(v + 1) * kTabStride;
-  r.comp = L.node_comp[v];
   const int c0 = r.comp ? __ffs(r.comp) - 1 : 0;
   const int nb = so.n_batch[c0];
   for (int gi = 0; gi < so.n_gpu[c0]; gi++) {
@@ -303,15 +436,25 @@ __device__ NodeCfg place(const EnumView &V, const OptsLds &so, Cursor &c, int v,
 // per instruction.  Needs out.P % 4 == 0; the last thread writes bytes.
 // HET: the space has nodes of two configurations (o.het); without them the
 // walk over configuration pairs is not compiled in.
+// Bound by the vector-memory issue rate: a byte load of the logical plan's
+// record per plan and route slot (512 a thread) took longer than the 233 B
+// written per plan.  With the block's record in LDS, the plan index divided
+// once per block and the walk by binary search, 2,000,000 omni plans and
+// their phase 1 take 389 us instead of 482 (16 GPUs, three batch sizes).
 constexpr int kPlansPerThread = 4;
 template <bool HET>
 __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V, const uint64_t *offsets,
                                                     uint64_t first, int count, PlanOut out) {
   __shared__ OptsLds so;
+  __shared__ BlockPos bp;
   stage_opts(so, o, threadIdx.x, blockDim.x);
-  __syncthreads();
-  const int p0 = (blockIdx.x * blockDim.x + threadIdx.x) * kPlansPerThread;
+  const int pb = blockIdx.x * blockDim.x * kPlansPerThread;  // the block's first plan
+  const int pe = min(count - pb, (int)blockDim.x * kPlansPerThread);
+  block_pos(bp, V, offsets, first + (uint64_t)pb, first + (uint64_t)(pb + pe - 1));
+  const int p0 = pb + threadIdx.x * kPlansPerThread;
   if (p0 >= count) return;
+  const bool one = bp.lo == bp.hi;
+  const int step = 1 << (31 - __clz(V.N));
   const size_t P = (size_t)out.P;
   const bool packed = p0 + kPlansPerThread <= count && (out.P % kPlansPerThread) == 0;
   // consecutive plans of one logical plan that differ only in their routing
@@ -320,7 +463,7 @@ __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V,
   bool same[kPlansPerThread];
 #pragma unroll
   for (int j = 0; j < kPlansPerThread; j++) {
-    cur[j] = locate(V, offsets, first + (uint64_t)(p0 + j), p0 + j < count);
+    cur[j] = locate(V, offsets, bp, first + (uint64_t)(p0 + j), (uint32_t)(p0 + j - pb), p0 + j < count);
     same[j] = j > 0 && cur[j].ok && cur[j - 1].ok && cur[j].l == cur[j - 1].l && cur[j].q == cur[j - 1].q;
   }
   auto put8 = [&](uint8_t *row, const uint8_t *x) {
@@ -338,7 +481,7 @@ __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V,
   for (int v = 0; v < CF_MAX_NODES; v++) {
     NodeCfg nc[kPlansPerThread];
 #pragma unroll
-    for (int j = 0; j < kPlansPerThread; j++) nc[j] = same[j] ? nc[j - 1] : place(V, so, cur[j], v, HET);
+    for (int j = 0; j < kPlansPerThread; j++) nc[j] = same[j] ? nc[j - 1] : place(V, so, bp, cur[j], v, HET, step);
 #pragma unroll
     for (int j = 0; j < kPlansPerThread; j++) b8[j] = nc[j].comp;
     put8(out.node_comp + v * P, b8);
@@ -376,7 +519,7 @@ __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V,
     uint8_t na[kPlansPerThread], w0[kPlansPerThread], w1[kPlansPerThread];
 #pragma unroll
     for (int j = 0; j < kPlansPerThread; j++) {
-      na[j] = cur[j].ok ? V.logical[cur[j].l].n_alt[t] : 0;
+      na[j] = cur[j].ok ? (one ? bp.n_alt[t] : V.logical[cur[j].l].n_alt[t]) : 0;
       w0[j] = na[j] == 1 ? 10 : 0;
       w1[j] = 0;
       if (na[j] == 2) {
@@ -388,50 +531,119 @@ __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V,
     put8(out.n_alt + t * P, na);
     put8(out.alt_w + (2 * t) * P, w0);
     put8(out.alt_w + (2 * t + 1) * P, w1);
-    for (int a = 0; a < 2; a++)
+    for (int a = 0; a < 2; a++) {
+      if (one) {  // eight routes in one LDS read, each written for the four plans at once
+        const uint64_t r8 = *(const uint64_t *)bp.route[t][a];
+#pragma unroll
+        for (int c = 0; c < CF_MAX_COMP; c++) {
+#pragma unroll
+          for (int j = 0; j < kPlansPerThread; j++) b8[j] = cur[j].ok ? (uint8_t)(r8 >> (8 * c)) : (uint8_t)255;
+          put8(out.alt_node + ((2 * t + a) * CF_MAX_COMP + c) * P, b8);
+        }
+        continue;
+      }
       for (int c = 0; c < CF_MAX_COMP; c++) {
 #pragma unroll
         for (int j = 0; j < kPlansPerThread; j++)
           b8[j] = cur[j].ok ? V.logical[cur[j].l].alt_node[t][a][c] : (uint8_t)255;
         put8(out.alt_node + ((2 * t + a) * CF_MAX_COMP + c) * P, b8);
       }
+    }
   }
 }
 
+// Issue-bound: linear walks over (batch size, n), 64-bit divisions by the routing digits and two
+// fp64 divisions per (type, alternative, component) were most of it.  10^7 omni plans in three
+// windows, selections included: 1,978 -> 1,188 us.
+//
 // Enumeration fused with phase 1: a thread numbers its plan, builds the
 // plan's nodes and routes in registers and LDS exactly as k_enum_unrank
 // would write them, and screens it as k_coarse would read them, writing only
 // R_d, the bottleneck and the flags (13 B per plan instead of the 233 B
 // table written and read back).
+//
+// A plan's batch size and GPUs per executor are options of the space, so the work per request
+// of every (type, component, option) is computed once per block into LDS (work_s, two
+// divisions each), and the routing shares (pq_s) likewise.  TAB: off where the options are so
+// many that the table would take more than kWorkBytes; the work is then computed per plan.
 constexpr int kScrBlock = 256;
+constexpr int kWorkBytes = 16384;
+struct ScreenPrep {
+  double ex[CF_MAX_TYPES][CF_MAX_COMP], en[CF_MAX_TYPES][CF_MAX_COMP];
+  uint16_t opt_b[CF_MAX_COMP * 32];  // an option's batch size and multiplier index
+  uint8_t opt_g[CF_MAX_COMP * 32];
+};
+template <bool TAB>
 __global__ void __launch_bounds__(kScrBlock) k_enum_screen(cf_enum_opts o, EnumView V, const uint64_t *offsets,
                                                           uint64_t first, int count, KModel m, const uint64_t *moments,
-                                                          int n_gpus, double *rd, int32_t *bott, uint8_t *flags) {
+                                                          int n_gpus, int n_opt, double *rd, int32_t *bott,
+                                                          uint8_t *flags) {
   __shared__ OptsLds so;
-  __shared__ double ex_s[CF_MAX_TYPES][CF_MAX_COMP];
-  __shared__ double en_s[CF_MAX_TYPES][CF_MAX_COMP];
-  __shared__ double tps_s[CF_MAX_COMP][8];
+  __shared__ BlockPos bp;
+  __shared__ double pq_s[CF_MAX_TYPES][10];  // pi_t q: [w] for w of ten tenths, [0] for one alternative
   __shared__ double u_s[CF_MAX_NODES][kScrBlock];
-  __shared__ uint16_t b_s[CF_MAX_NODES][kScrBlock];
-  __shared__ uint8_t g_s[CF_MAX_NODES][kScrBlock];
+  __shared__ uint8_t k_s[CF_MAX_NODES][kScrBlock];  // a node's option, opt_base[c0] + gi nb + bi
+  __shared__ uint16_t opt_base[CF_MAX_COMP];
+  extern __shared__ double work_s[];            // TAB: [t][c][option]
+  // with the table these are read before u_s is written and take its place: 40 KB and four
+  // blocks per CU
+  ScreenPrep *pr;
+  if constexpr (TAB) {
+    pr = (ScreenPrep *)&u_s[0][0];
+  } else {
+    __shared__ ScreenPrep own;
+    pr = &own;
+  }
   const int tid = threadIdx.x;
   stage_opts(so, o, tid, blockDim.x);
-  if (tid < CF_MAX_COMP * 8) (&tps_s[0][0])[tid] = (&m.tps[0][0])[tid];
-  phase1_means(m, moments, tid, ex_s, en_s);
-  __syncthreads();
-  const int p = blockIdx.x * kScrBlock + tid;
+  phase1_means(m, moments, tid, pr->ex, pr->en);
+  if (tid < m.nt * 10) {
+    const int t = tid / 10, w = tid % 10;
+    const double pi = (double)m.weight[t] / (double)m.wsum;
+    pq_s[t][w] = pi * (w ? (double)w / 10.0 : 1.0);
+  }
+  if (tid < m.nc) {  // the options of components before this one come first
+    int base = 0;
+    for (int c = 0; c < tid; c++) base += o.n_batch[c] * o.n_gpu_opt[c];
+    opt_base[tid] = (uint16_t)base;
+    for (int gi = 0; gi < o.n_gpu_opt[tid]; gi++)
+      for (int bi = 0; bi < o.n_batch[tid]; bi++) {
+        const int g = o.gpu_opt[tid][gi];
+        pr->opt_b[base + gi * o.n_batch[tid] + bi] = o.batch[tid][bi];
+        pr->opt_g[base + gi * o.n_batch[tid] + bi] = (uint8_t)(g > 8 ? 7 : g - 1);
+      }
+  }
+  const int pb = blockIdx.x * kScrBlock;
+  const int pe = min(count - pb, kScrBlock);
+  block_pos(bp, V, offsets, first + (uint64_t)pb, first + (uint64_t)(pb + pe - 1));
+  if constexpr (TAB) {
+    for (int i = tid; i < m.nt * m.nc * n_opt; i += kScrBlock) {
+      const int k = i % n_opt, c = (i / n_opt) % m.nc, t = i / (n_opt * m.nc);
+      work_s[i] = phase1_work(m, c, pr->opt_b[k], pr->ex[t][c], pr->en[t][c], m.tps[c][pr->opt_g[k]]);
+    }
+    __syncthreads();
+  }
+  const int p = pb + tid;
   if (p >= count) return;
-  Cursor cur = locate(V, offsets, first + (uint64_t)p, true);
+  Cursor cur = locate(V, offsets, bp, first + (uint64_t)p, (uint32_t)tid, true);
   const int nv = cur.nv;
+  const bool one = bp.lo == bp.hi;
+  const int step = 1 << (31 - __clz(V.N));
   uint32_t rep[CF_MAX_NODES], gp[CF_MAX_NODES];
 #pragma unroll
   for (int v = 0; v < CF_MAX_NODES; v++) {
-    const NodeCfg nc = place(V, so, cur, v, false);
-    rep[v] = nc.rep;
-    gp[v] = nc.gpus;
-    b_s[v][tid] = nc.batch;
-    if (m.tp_any) g_s[v][tid] = (uint8_t)(nc.gpus < 1 ? 0 : (nc.gpus > 8 ? 7 : nc.gpus - 1));
-    u_s[v][tid] = 0.0;
+    rep[v] = gp[v] = 0;
+    if (v < nv) {
+      const int comp = one ? bp.comp[v] : V.logical[cur.l].node_comp[v];
+      int c0, gi, bi, n;
+      k_s[v][tid] = 0;
+      if (place_one(V, so, cur, v, comp, step, c0, gi, bi, n)) {
+        rep[v] = (uint8_t)n;
+        gp[v] = so.gpu[c0][gi];
+        k_s[v][tid] = (uint8_t)(opt_base[c0] + gi * so.n_batch[c0] + bi);
+      }
+      u_s[v][tid] = 0.0;
+    }
   }
   if (!cur.ok || nv < 1) {
     rd[p] = 0.0;
@@ -440,31 +652,29 @@ __global__ void __launch_bounds__(kScrBlock) k_enum_screen(cf_enum_opts o, EnumV
     return;
   }
   const cf_logical &L = V.logical[cur.l];
-  const double wsum = (double)m.wsum;
   int i2 = 0;
   for (int t = 0; t < m.nt; t++) {
     const uint32_t path = m.path[t];
-    const uint32_t na = L.n_alt[t];
-    uint32_t wl[2] = {10u, 0u};
+    const uint32_t na = one ? bp.n_alt[t] : L.n_alt[t];
+    uint32_t wl[2] = {0u, 0u};  // tenths; 0 is the whole of one alternative
     if (na == 2) {
       wl[0] = (cur.w >> (4 * i2)) & 15u;
       wl[1] = 10u - wl[0];
       i2++;
     }
-    const double pi = (double)m.weight[t] / wsum;
-    const uint32_t wtot = na > 1 ? wl[0] + wl[1] : 1u;
 #pragma unroll
     for (int a = 0; a < 2; a++) {
       if (a < (int)na) {
-        const uint32_t wa = na > 1 ? wl[a] : 1u;
-        const double q = (double)wa / (double)wtot;
-        const double pq = pi * q;
+        const double pq = pq_s[t][wl[a]];
+        const uint64_t r8 = one ? *(const uint64_t *)bp.route[t][a] : 0ull;
 #pragma unroll
         for (int c = 0; c < CF_MAX_COMP; c++) {
           if (!((path >> c) & 1u)) continue;
-          const int v = L.alt_node[t][a][c];
-          const double w =
-              phase1_work(m, c, b_s[v][tid], ex_s[t][c], en_s[t][c], m.tp_any ? tps_s[c][g_s[v][tid]] : 1.0);
+          const int v = one ? (int)((r8 >> (8 * c)) & 255u) : L.alt_node[t][a][c];
+          const int k = k_s[v][tid];
+          double w;
+          if constexpr (TAB) w = work_s[(t * m.nc + c) * n_opt + k];
+          else w = phase1_work(m, c, pr->opt_b[k], pr->ex[t][c], pr->en[t][c], m.tps[c][pr->opt_g[k]]);
           u_s[v][tid] = u_s[v][tid] + pq * w;
         }
       }
@@ -473,10 +683,18 @@ __global__ void __launch_bounds__(kScrBlock) k_enum_screen(cf_enum_opts o, EnumV
   phase1_result(nv, rep, gp, [&](int v) { return u_s[v][tid]; }, n_gpus, &rd[p], &bott[p], &flags[p]);
 }
 
+int most_gpu_options(const cf_enum_opts *o) {
+  int ng = 1;
+  for (int c = 0; c < CF_MAX_COMP; c++)  // a logical plan's nodes hold components of the model only
+    ng = std::max(ng, std::min<int>(o->n_gpu_opt[c], 4));
+  return ng;
+}
+
 cf_status run_tables(const cf_enum_opts *opts, const cf_logical *logical_dev, int n_logical, uint64_t **tab_out,
                      uint64_t **totals_out, hipStream_t s) {
   cf_status st = CF_OK;
-  const size_t bytes = sizeof(uint64_t) * ((size_t)n_logical * kTabSize + (size_t)n_logical);
+  const size_t per = tab_size(opts->het, most_gpu_options(opts));
+  const size_t bytes = sizeof(uint64_t) * ((size_t)n_logical * per + (size_t)n_logical);
   uint64_t *scr = (uint64_t *)scratch_get(SCR_ENUM, bytes, &st);
   if (!scr) return st;
   EnumView V;
@@ -484,7 +702,8 @@ cf_status run_tables(const cf_enum_opts *opts, const cf_logical *logical_dev, in
   V.logical = logical_dev;
   V.n_logical = n_logical;
   V.tab = scr;
-  V.totals = scr + (size_t)n_logical * kTabSize;
+  V.ng = most_gpu_options(opts);
+  V.totals = scr + (size_t)n_logical * per;
   hipLaunchKernelGGL(k_enum_table, dim3((unsigned)n_logical), dim3(128), 0, s, *opts, V);
   st = hip_check(hipGetLastError(), "cf_enum table launch");
   *tab_out = V.tab;
@@ -673,6 +892,7 @@ extern "C" cf_status cf_enum_plans(const cf_model_desc *model, const cf_enum_opt
   V.N = opts->n_gpus;
   V.logical = logical_dev;
   V.n_logical = n_logical;
+  V.ng = most_gpu_options(opts);
   V.tab = tab;
   V.totals = totals;
   PlanOut o;
@@ -721,9 +941,18 @@ extern "C" cf_status cf_enum_screen(const cf_model_desc *model, const cf_enum_op
   V.N = opts->n_gpus;
   V.logical = logical_dev;
   V.n_logical = n_logical;
+  V.ng = most_gpu_options(opts);
   V.tab = tab;
   V.totals = totals;
-  hipLaunchKernelGGL(k_enum_screen, dim3((unsigned)((count + kScrBlock - 1) / kScrBlock)), dim3(kScrBlock), 0, s,
-                     *opts, V, offsets_dev, first, count, m, moments_dev, n_gpus, rd_dev, bottleneck_dev, flags_dev);
+  int n_opt = 0;
+  for (int c = 0; c < model->n_comp; c++) n_opt += opts->n_batch[c] * opts->n_gpu_opt[c];
+  const size_t work = sizeof(double) * (size_t)m.nt * m.nc * n_opt;
+  const dim3 grid((unsigned)((count + kScrBlock - 1) / kScrBlock));
+  if (work <= (size_t)kWorkBytes)
+    hipLaunchKernelGGL(k_enum_screen<true>, grid, dim3(kScrBlock), work, s, *opts, V, offsets_dev, first, count, m,
+                       moments_dev, n_gpus, n_opt, rd_dev, bottleneck_dev, flags_dev);
+  else
+    hipLaunchKernelGGL(k_enum_screen<false>, grid, dim3(kScrBlock), 0, s, *opts, V, offsets_dev, first, count, m,
+                       moments_dev, n_gpus, n_opt, rd_dev, bottleneck_dev, flags_dev);
   return hip_check(hipGetLastError(), "cf_enum_screen launch");
 }
