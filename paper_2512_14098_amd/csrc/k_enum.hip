@@ -552,10 +552,6 @@ __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V,
   }
 }
 
-// Issue-bound: linear walks over (batch size, n), 64-bit divisions by the routing digits and two
-// fp64 divisions per (type, alternative, component) were most of it.  10^7 omni plans in three
-// windows, selections included: 1,978 -> 1,188 us.
-//
 // Enumeration fused with phase 1: a thread numbers its plan, builds the
 // plan's nodes and routes in registers and LDS exactly as k_enum_unrank
 // would write them, and screens it as k_coarse would read them, writing only
@@ -566,6 +562,9 @@ __global__ void __launch_bounds__(256) k_enum_unrank(cf_enum_opts o, EnumView V,
 // of every (type, component, option) is computed once per block into LDS (work_s, two
 // divisions each), and the routing shares (pq_s) likewise.  TAB: off where the options are so
 // many that the table would take more than kWorkBytes; the work is then computed per plan.
+// Issue-bound: linear walks over (batch size, n), 64-bit divisions by the routing digits and two
+// fp64 divisions per term were most of it.  10^7 omni plans in three windows, selections
+// included: 1,978 -> 1,188 us.
 constexpr int kScrBlock = 256;
 constexpr int kWorkBytes = 16384;
 struct ScreenPrep {
@@ -685,8 +684,7 @@ __global__ void __launch_bounds__(kScrBlock) k_enum_screen(cf_enum_opts o, EnumV
 
 int most_gpu_options(const cf_enum_opts *o) {
   int ng = 1;
-  for (int c = 0; c < CF_MAX_COMP; c++)  // a logical plan's nodes hold components of the model only
-    ng = std::max(ng, std::min<int>(o->n_gpu_opt[c], 4));
+  for (int c = 0; c < CF_MAX_COMP; c++) ng = std::max(ng, std::min<int>(o->n_gpu_opt[c], 4));
   return ng;
 }
 
