@@ -139,7 +139,8 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t &total) 
 // Device memory (global address space) addressed by a 32-bit byte offset
 // from a base held in scalar registers: loads and stores take the
 // scalar-base + vector-offset form, with no 64-bit address arithmetic per
-// lane.  Every array the kernel indexes is far below 4 GiB.
+// lane.  What is indexed this way is at most 4 GiB: parts of a wavefront's memory
+// and one seed's part of a trace array.
 #define CF_GLOBAL __attribute__((address_space(1)))
 template <typename T>
 struct GPtr {
@@ -156,10 +157,17 @@ __device__ __forceinline__ GPtr<T> gptr_at(char *base, size_t off) {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// element o of a read-only input array
+// element i of a trace array's part from element off on (wave-uniform: the
+// seed's first request).  The part's address is formed in 64 bits, because the
+// array may hold any number of seeds; i is a request of one seed, at most 2^26
+// elements of 8 bytes, so that its offset fits 32 bits.
 template <typename T>
-__device__ __forceinline__ T gload(const T *p, size_t o) {
-  return *(const CF_GLOBAL T *)((const CF_GLOBAL char *)p + (uint32_t)o * (uint32_t)sizeof(T));
+__device__ __forceinline__ T gload(const T *p, size_t off, uint32_t i) {
+  const CF_GLOBAL char *part = (const CF_GLOBAL char *)(p + off);
+  // kept in scalar registers: without this the compiler adds offsets per lane
+  // (24 triples of 1,000 requests 7.95 ms, with it 7.77)
+  asm("" : "+s"(part));
+  return *(const CF_GLOBAL T *)(part + i * (uint32_t)sizeof(T));
 }
 
 // k_fine_reg.hip: the simulator with its whole control state in registers, for

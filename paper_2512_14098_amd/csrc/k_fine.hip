@@ -352,7 +352,7 @@ __device__ __forceinline__ uint32_t nout_of(const Sim &S, uint32_t r, int t, int
   return v < 1 ? 1 : v;
 }
 __device__ __forceinline__ double arrival_time(const Sim &S, uint32_t r) {
-  return ((double)gload(S.A->ticks, S.soff + r) * 0x1p-32) / S.lam;
+  return ((double)gload(S.A->ticks, S.soff, r) * 0x1p-32) / S.lam;
 }
 __device__ __forceinline__ int ex_byte(uint64_t ex, int c) { return (int)((ex >> (8 * c)) & 0xFFu); }
 __device__ __forceinline__ int rtype(uint32_t misc) { return (int)((misc >> 8) & 7u); }
@@ -680,13 +680,13 @@ __device__ void arrive(Sim &S, uint32_t r) {
   const FineArgs &A = *S.A;
   const WaveShared &sh = *S.sh;
   S.events++;
-  const size_t o = S.soff + r;
+  const size_t o = S.soff;
   // every field of the request is loaded before any is used (one memory latency)
-  const uint8_t tv = gload(A.type, o);
-  const uint64_t k0v = gload(A.rkey0, o), k1v = gload(A.rkey1, o);
-  const uint32_t akv = gload(A.akey, o);
-  const uint16_t prv = gload(A.prompt, o), ouv = gload(A.out, o), pav = gload(A.patches, o);
-  const uint32_t aiv = gload(A.aud_in, o), aov = gload(A.aud_out, o);
+  const uint8_t tv = gload(A.type, o, r);
+  const uint64_t k0v = gload(A.rkey0, o, r), k1v = gload(A.rkey1, o, r);
+  const uint32_t akv = gload(A.akey, o, r);
+  const uint16_t prv = gload(A.prompt, o, r), ouv = gload(A.out, o, r), pav = gload(A.patches, o, r);
+  const uint32_t aiv = gload(A.aud_in, o, r), aov = gload(A.aud_out, o, r);
   const int t = ri(tv);
   if (t >= m.nt) {
     S.status |= CF_ST_INVALID;
@@ -777,7 +777,7 @@ __device__ void members_done(Sim &S, int x, int si, int c, int kind, int n, GPtr
       r = rs ? (*rs)[j] : mem[j];
       // loads that depend on the request id only, issued with its record
       R = rec_get(S, r);
-      tkv = gload(S.A->ticks, S.soff + r);
+      tkv = gload(S.A->ticks, S.soff, r);
       if (kind == IT_PREFILL) a_no = attr(S, r, ml.nout_attr[c]);
     }
     const int t = rtype(R.misc);
@@ -1972,7 +1972,7 @@ __global__ void __launch_bounds__(64, G ? 4 : 7) k_fine(const FineArgs *__restri
         }
         while (next_arr < (uint32_t)A.n && S.t_arr == t) {
           // the next arrival's time is loaded while this one is handled
-          const uint64_t tk = next_arr + 1u < (uint32_t)A.n ? gload(A.ticks, S.soff + next_arr + 1u) : 0ull;
+          const uint64_t tk = next_arr + 1u < (uint32_t)A.n ? gload(A.ticks, S.soff, next_arr + 1u) : 0ull;
           arrive<G>(S, next_arr);
           next_arr++;
           S.t_arr = next_arr < (uint32_t)A.n ? rdb(((double)tk * 0x1p-32) / S.lam) : __builtin_inf();

@@ -73,7 +73,7 @@ struct Reg {
   CF_GLOBAL char *slab;
   uint32_t o_run, o_mem, o_dl, o_pool, o_next, o_free;
   GPtr<const uint64_t> ticks;  // the seed's arrival ticks
-  size_t soff;
+  uint32_t seed;
   double lam, now, dl_head_t, comm;
   uint64_t events, dirty, busy, runm, done_now;  // executor masks: busy, in a multi-step decode run, ended at `now`
   uint32_t status, dl_head, dl_tail, dl_mask;
@@ -234,15 +234,15 @@ __device__ __forceinline__ void load_arrivals(Reg &S, uint32_t base) {
   S.a_ex = ~0ull;
   S.a_type = CF_MAX_TYPES;
   if (r < (uint32_t)A.n) {
-    const size_t o = S.soff + r;
-    const uint64_t tk = gload(A.ticks, o);
-    const uint32_t t = gload(A.type, o), ak = gload(A.akey, o);
-    const uint64_t k0 = gload(A.rkey0, o), k1 = gload(A.rkey1, o);
+    const size_t o = (size_t)S.seed * (size_t)A.n;
+    const uint64_t tk = S.ticks[r];
+    const uint32_t t = gload(A.type, o, r), ak = gload(A.akey, o, r);
+    const uint64_t k0 = gload(A.rkey0, o, r), k1 = gload(A.rkey1, o, r);
     u32x4 w;
-    w.x = (uint32_t)gload(A.prompt, o) | ((uint32_t)gload(A.out, o) << 16);
-    w.y = gload(A.patches, o);
-    w.z = gload(A.aud_in, o);
-    w.w = gload(A.aud_out, o);
+    w.x = (uint32_t)gload(A.prompt, o, r) | ((uint32_t)gload(A.out, o, r) << 16);
+    w.y = gload(A.patches, o, r);
+    w.z = gload(A.aud_in, o, r);
+    w.w = gload(A.aud_out, o, r);
     S.a_t = ((double)tk * 0x1p-32) / S.lam;
     if (t < (uint32_t)m.nt) {
       int alt = 0;
@@ -836,8 +836,8 @@ __global__ void __launch_bounds__(64, 6) k_fine_reg(const FineArgs *__restrict__
     }
     const int p = ri(A.plan_ids[i]);
     const size_t oidx = ((size_t)i * A.K + k) * A.S + s;
-    S.soff = (size_t)s * A.n;
-    S.ticks = GPtr<const uint64_t>{(const CF_GLOBAL uint64_t *)(A.ticks + S.soff)};
+    S.seed = (uint32_t)s;
+    S.ticks = GPtr<const uint64_t>{(const CF_GLOBAL uint64_t *)(A.ticks + (size_t)s * A.n)};
     S.lam = rdb(A.rates[(size_t)i * A.K + k]);
     S.events = 0;
     S.status = 0;
