@@ -200,15 +200,40 @@ __global__ void __launch_bounds__(kDraw) k_trace_draw(KModel m, SeedChunk seeds,
 // ---- exact u64 inclusive scan of each seed's gaps: the draw leaves the sums
 // inside its blocks and the blocks' totals; those are scanned per seed and
 // added back.
-__global__ void __launch_bounds__(64) k_scan_totals(uint64_t *tot, int nb) {
-  const int s = blockIdx.x, lane = threadIdx.x;
+// One block per seed; a round scans kTotBlock * kTotPer totals, and the rounds
+// depend on each other, so a block takes as many totals at once as it can hold:
+// with one wavefront and 64 totals a round, generating one trace of 2^26
+// requests (262,144 totals) took 9.53 ms, now 7.32; 2^20 requests 181 -> 153 us.
+constexpr int kTotBlock = 1024, kTotPer = 4;
+__global__ void __launch_bounds__(kTotBlock) k_scan_totals(uint64_t *tot, int nb) {
+  __shared__ uint64_t wsum[kTotBlock / 64];
+  const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint64_t carry = 0;
   uint64_t *t = tot + (size_t)s * nb;
-  for (int b0 = 0; b0 < nb; b0 += 64) {
-    uint64_t v = (b0 + lane < nb) ? t[b0 + lane] : 0;
-    uint64_t incl = wave_incl_scan(v, lane);
-    if (b0 + lane < nb) t[b0 + lane] = carry + incl - v;  // exclusive
-    carry += __shfl(incl, 63, 64);
+  for (int b0 = 0; b0 < nb; b0 += kTotBlock * kTotPer) {
+    const int i0 = b0 + tid * kTotPer;
+    uint64_t v[kTotPer], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kTotPer; j++) {
+      v[j] = i0 + j < nb ? t[i0 + j] : 0;
+      sum += v[j];
+    }
+    const uint64_t incl = wave_incl_scan(sum, lane);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint64_t e = carry + incl - sum;  // exclusive
+#pragma unroll
+    for (int k = 0; k < kTotBlock / 64; k++) {
+      const uint64_t x = wsum[k];
+      if (k < wave) e += x;
+      carry += x;
+    }
+#pragma unroll
+    for (int j = 0; j < kTotPer; j++) {
+      if (i0 + j < nb) t[i0 + j] = e;
+      e += v[j];
+    }
+    __syncthreads();  // the wavefronts' sums are read before the next round writes them
   }
 }
 
@@ -258,7 +283,7 @@ extern "C" cf_status cf_trace_gen(const cf_model_desc *model, const uint64_t *se
                        moments_dev, tot, nb);
   }
   if (nb > 1) {  // one block's sums need nothing added
-    hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)n_seeds), dim3(64), 0, s, tot, nb);
+    hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)n_seeds), dim3(kTotBlock), 0, s, tot, nb);
     hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((nb + kAddPer - 1) / kAddPer), (unsigned)n_seeds), dim3(kDraw), 0, s,
                        out->arr_ticks_dev, n_req, tot, nb);
   }

@@ -20,9 +20,7 @@ MODEL = model(
      rtype("c", ["L"], weight=1)])
 
 
-@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 1024, 1025, 3000])
-@pytest.mark.parametrize("seeds", [[5], [6, 2 ** 63 + 1, 7]])
-def test_trace_block_edges(n, seeds):
+def _check(n, seeds):
     from paper_2512_14098_amd import cf
     tr, mom = cf.cf_trace_gen(cf.model_desc(MODEL), seeds, n)
     want = O.trace_gen(O.make_model(MODEL), seeds, n)
@@ -30,3 +28,17 @@ def test_trace_block_edges(n, seeds):
     for f, _ in cf.TRACE_FIELDS:
         assert np.array_equal(got[f], want[f]), (f, n)
     assert np.array_equal(mom.cpu().numpy().view(np.uint64), want["moments"])
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 1024, 1025, 3000])
+@pytest.mark.parametrize("seeds", [[5], [6, 2 ** 63 + 1, 7]])
+def test_trace_block_edges(n, seeds):
+    _check(n, seeds)
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 255, 1 << 20, (1 << 20) + 1, (1 << 21) + 300])
+def test_block_totals_over_one_round(n):
+    """4,096 block totals are scanned in one round: one round just full, the second with one
+    total, the third with two."""
+    print(f"trace totals: {n} requests", flush=True)
+    _check(n, [5, 9])
