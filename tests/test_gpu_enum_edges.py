@@ -55,3 +55,29 @@ def test_enumeration_edges(name, N, batch, gpus):
         w = O.eval_coarse(m, want, mom_h, N)
         assert np.array_equal(rd.cpu().numpy(), w[0]) and np.array_equal(bn.cpu().numpy(), w[1]), (first, cnt)
         assert np.array_equal(fl.cpu().numpy(), w[2]), (first, cnt)
+
+
+def test_enumeration_after_a_count_finds_its_scratch():
+    """cf_enum_count keeps no table but sizes the scratch for one: the enumeration that follows
+    allocates no device memory (it may be under stream capture)."""
+    from paper_2512_14098_amd import cf
+    mc = load_config("c2")["model"]
+    spec = {"k_s": 2, "share": True, "batch": {c["name"]: [16, 64] for c in mc["components"]},
+            "gpus": {c["name"]: [1, 2, 4, 8] for c in mc["components"]}}
+    desc, opts = cf.model_desc(mc), cf.enum_opts(mc, spec, 12)
+    ldev = torch.from_numpy(cf.cf_enum_logical(desc, opts)).cuda()
+    tab = cf.DevicePlans.empty(1000)
+    mom = cf.cf_trace_gen(desc, [3], 100)[1]
+    cf.cf_enum_screen(desc, opts, ldev, *cf.cf_enum_count(desc, opts, ldev), 0, 1000, mom[0], 12)  # code loaded
+    torch.cuda.synchronize()
+    cf.cf_release_scratch()
+    offsets, total = cf.cf_enum_count(desc, opts, ldev)
+    free = torch.cuda.mem_get_info()[0]
+    cf.cf_enum_plans(desc, opts, ldev, offsets, total, 0, 1000, tab)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free
+    m, oo = O.make_model(mc), O.enum_opts(mc, spec, 12)
+    want = O.enum_plans(m, oo, O.enum_logical(m, oo), 0, 1000)
+    got = tab.to_host()
+    for f in PlanTable.FIELDS:
+        assert np.array_equal(getattr(got, f), getattr(want, f)), f
