@@ -6,8 +6,9 @@ Plan tables come from the workloads' sampler with second configurations switched
 (``het``), some nodes given two-GPU second configurations under a tensor-parallel
 multiplier; phase 1 (R_d, bottleneck, flags), phase 2 (counts, goodput, every sampled
 latency) and phase 3 (counts, events, status of every triple, latencies of whole triples)
-are compared with the oracle bit for bit, for a model without gating (c1, k_fine<false>)
-and the omni model (c2, k_fine<true>).
+are compared with the oracle bit for bit, for a model without gating (c1) and the omni model
+(c2).  Phase 3 of both runs in the simulators with their control state in registers; the
+general ones have their plans of two configurations in test_gpu_fine_general.py.
 """
 import copy
 
