@@ -369,7 +369,10 @@ cf_status cf_pareto(const double *goodput_t_dev, int32_t n, int32_t T, uint8_t *
  * colocatable edges (bit c of colocatable[p]: the edge p -> c may be
  * merged), and per component its batch knobs (1..8 values in 1..256) and
  * GPUs-per-executor options (1..4 values in 1..N); a node takes the options
- * of its lowest component. */
+ * of its lowest component.  The count, enumeration and screening calls keep a
+ * table in the library's scratch: 8.3 KB per logical plan and GPU option of the
+ * component with most of them (33 KB per logical plan at four), or 8.8 KB per
+ * logical plan where nodes may take two configurations. */
 typedef struct cf_enum_opts {
   int32_t n_gpus;
   int32_t k_s;

@@ -67,10 +67,10 @@ __global__ void __launch_bounds__(HET ? kBlockGroups : kBlock)
   if (p >= pv.P) return;
   const size_t P = (size_t)pv.P;
 #define AT(arr, slot) (arr)[(size_t)(slot) * P + (size_t)p]
-  // Every field the plan's evaluation needs is loaded first, with no load
-  // depending on another (one memory latency per plan instead of one per
-  // field); slots past the plan's node count and alternatives past its
-  // count are not fetched.
+  // A plan's node fields and its first type's routes are loaded first, then the
+  // routes of each next type while one is summed, with no load depending on
+  // another but on the node count: slots past it are not fetched, while both
+  // alternatives of a type always are.
   const int nv = pv.n_nodes[p];
   auto fetch = [&](int t, Routes &r) {
     const uint32_t path = m.path[t];

@@ -98,7 +98,8 @@ struct EnumView {
   uint64_t *totals;   // [n_logical]
 };
 
-// u64 entries of one logical plan's table
+// u64 entries of one logical plan's table: 8.8 KB with second configurations, else 8.3 KB per GPU
+// option (33 KB for four)
 __host__ __device__ __forceinline__ size_t tab_size(bool het, int ng) {
   return het ? (size_t)kTabSize : (size_t)CF_MAX_NODES * ng * kTabStride;
 }
@@ -587,8 +588,9 @@ __global__ void __launch_bounds__(kScrBlock) k_enum_screen(cf_enum_opts o, EnumV
   __shared__ uint8_t k_s[CF_MAX_NODES][kScrBlock];  // a node's option, opt_base[c0] + gi nb + bi
   __shared__ uint16_t opt_base[CF_MAX_COMP];
   extern __shared__ double work_s[];            // TAB: [t][c][option]
-  // with the table these are read before u_s is written and take its place: 40 KB and four
-  // blocks per CU
+  // with the table these are read before u_s is written and take its place: 38 KB and the
+  // table (2.4 KB for the omni model with three batch sizes and one GPU option, four blocks per
+  // CU; at most 16 KB, two blocks)
   ScreenPrep *pr;
   if constexpr (TAB) {
     pr = (ScreenPrep *)&u_s[0][0];

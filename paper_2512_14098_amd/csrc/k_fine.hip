@@ -36,9 +36,10 @@
 // Two instantiations of the kernel: k_fine<false> simulates thinker steps
 // one at a time and wakes the talker executors after every remote thinker
 // step; it serves models without a gated stage, where none of that is
-// reached, whose plans have more than 64 stage instances (k_fine_reg.hip
-// takes the others).  k_fine<true>, used for models with a gated stage, also runs
-// thinker stages in decode runs and replaces the per-step wake-ups by exact
+// reached, in launches of which some plan has more than 64 stage instances
+// (k_fine_reg.hip takes the others).  k_fine<true>, used for models with a gated
+// stage and LLM components besides it and its gate source (k_fine_gate.hip takes
+// those without), also runs thinker stages in decode runs and replaces the per-step wake-ups by exact
 // wake times: a talker request becomes eligible at the visibility time of
 // the thinker token it waits for, the only state change not caused by an
 // event of its own executor.  An executor hosting a talker stage that is

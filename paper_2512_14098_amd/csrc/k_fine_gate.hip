@@ -1135,8 +1135,8 @@ __device__ __forceinline__ void setup_model(Gate &S) {
   }
 }
 
-// 96 VGPRs with 12 spilled: 5 wavefronts per SIMD measure 495 ms on the launch
-// below, 4 (128 VGPRs) 563 ms, 6 (63 spilled) 586 ms.
+// 96 VGPRs, 5 wavefronts per SIMD (18 VGPRs and 204 SGPRs spilled): 495 ms on the
+// launch of 32,000 triples above; 4 (128 VGPRs) 563 ms, 6 (63 VGPRs spilled) 586 ms.
 __global__ void __launch_bounds__(64, 5) k_fine_gate(const FineArgs *__restrict__ Ap) {
   __shared__ GateLds sh;
   const int lane = lane_id();

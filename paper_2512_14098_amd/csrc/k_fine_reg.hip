@@ -4,10 +4,8 @@
 // words, for models without a gated stage and launches whose plans have at
 // most 64 stage instances.
 //
-// What bounds this simulator is instruction issue: with full occupancy the
-// scalar and the vector pipe are both busy about 85 % of the time, and a lone
-// wavefront still spends nearly half of its cycles issuing (the rest waiting
-// for LDS, the scalar cache and L2).  Control state in LDS is what costs the
+// What bounds this simulator is instruction issue (counters of a whole launch:
+// profiles/k_fine_c1.md).  Control state in LDS is what costs the
 // instructions: every uniform field that is read comes back in a vector
 // register, so that its arithmetic and its branches go through the vector
 // pipe and the execution mask.  Here
@@ -32,9 +30,7 @@
 // Measured against k_fine<false> on the same launches: 15,360 triples of 10^4
 // requests of the two-component model on 8 GPUs 535 -> 347 ms; 6,400 triples
 // of 5,000 text-to-image requests 90 -> 56 ms; 24 triples of 1,000 requests
-// (one wavefront per CU, latency only) 14.3 -> 7.9 ms.  Per instant 820 -> 530
-// instructions (of them 295 -> 184 vector, 34 -> 3 LDS, 9 -> 0 scalar loads),
-// before its branches were kept scalar.
+// (one wavefront per CU, latency only) 14.3 -> 7.9 ms.
 #include "cf_fine_reg.h"
 #include "cf_run.h"
 
@@ -788,8 +784,8 @@ __device__ __forceinline__ void setup_model(Reg &S) {
   }
 }
 
-// 80 VGPRs (6 wavefronts per SIMD, a few spills outside the event loop): 5 and
-// 7 per SIMD measure within 3 % on full launches, 7 is 4 % slower alone.
+// 80 VGPRs, 6 wavefronts per SIMD (8 VGPRs and 73 SGPRs spilled): 5 and 7 per
+// SIMD measure within 3 % on full launches, 7 is 4 % slower alone.
 __global__ void __launch_bounds__(64, 6) k_fine_reg(const FineArgs *__restrict__ Ap) {
   __shared__ RegLds sh;
   const int lane = lane_id();
