@@ -3,9 +3,10 @@
 A step is one pass of the whole evaluated path over one synthetic workload:
 trace generation, phase-1 screening of every plan, top-K selection, rate
 grid, phase-3 simulation of every (plan, rate, seed) triple, goodput
-reduction and selection.  Default workload: c1 (E->L on 8 simulated GPUs,
-1000 plans screened, the kept ones simulated at 16 rates x 32 seeds x 10^4
-requests).  Prints one JSON line.
+reduction and selection.  Default workload: c4 (omni graph on 64 simulated
+GPUs, 10^6 plans screened, the top 1000 simulated at 32 rates x 64 seeds x
+10^5 requests), whose step simulates every other selected plan at every rate
+on one seed.  Prints one JSON line.
 
 Other modes (each prints its own JSON line and exits): --enum times plan
 enumeration on the device, phase-1 screening of its output, the fused
@@ -50,28 +51,29 @@ _W_C3_SEED0 = ("c3: Text-to-image graph L -> 50-step diffusion G (1024^2) mixed 
 _W_C4_STEP = ("c4: Full coarse-to-fine sweep of the omni graph on 64 simulated GPUs: coarse screening of 10^6 "
               "sampled plans, the top 1000 by R_d simulated at 32 rates x 64 seeds x 100000 requests; each step: "
               "the trace of all 64 seeds, phase 1 over all 1000000 plans, the top 1000 and their 32-rate grid, "
-              "phase 3 of every selected plan at every rate on one seed (seed g at step g), their goodput reduction")
+              "phase 3 of every 2-th selected plan at every rate on one seed (plan slice g mod 2 of seed g div 2 "
+              "at step g), their goodput reduction")
 MEASURED_TRAFFIC = {
-    ("7ed4a4b598700ba3", _W_C4_STEP): 1.4861e13,
-    ("7ed4a4b598700ba3", _W_C1): 8.4908e11,
-    ("7ed4a4b598700ba3", _W_C2_SEEDS2): 7.9068e11,
-    ("7ed4a4b598700ba3", _W_C3_SEED0): 1.8009e12,
+    ("e4d12b7eed477dcc", _W_C4_STEP): 2.4697e13,
+    ("e4d12b7eed477dcc", _W_C1): 9.3816e11,
+    ("e4d12b7eed477dcc", _W_C2_SEEDS2): 2.2424e12,
+    ("e4d12b7eed477dcc", _W_C3_SEED0): 2.1163e12,
 }
-# VALU lane rate of the k_fine launch by rocprofv3 counters (SQ_INSTS_VALU x SQ_THREAD_CYCLES_VALU /
+# VALU lane rate of the simulation launch by rocprofv3 counters (SQ_INSTS_VALU x SQ_THREAD_CYCLES_VALU /
 # SQ_ACTIVE_INST_VALU / kernel time / PEAK_LANE_OPS), keyed like MEASURED_TRAFFIC
 MEASURED_LANE_FRAC = {
-    ("7ed4a4b598700ba3", _W_C4_STEP): 0.3829,
-    ("7ed4a4b598700ba3", _W_C1): 0.4314,
-    ("7ed4a4b598700ba3", _W_C2_SEEDS2): 0.4059,
-    ("7ed4a4b598700ba3", _W_C3_SEED0): 0.3950,
+    ("e4d12b7eed477dcc", _W_C4_STEP): 0.2856,
+    ("e4d12b7eed477dcc", _W_C1): 0.2817,
+    ("e4d12b7eed477dcc", _W_C2_SEEDS2): 0.3561,
+    ("e4d12b7eed477dcc", _W_C3_SEED0): 0.2689,
 }
 ENUM_KERNEL_SOURCES = ("paper_2512_14098_amd/csrc/k_enum.hip", "paper_2512_14098_amd/csrc/cf_internal.h",
                        "paper_2512_14098_amd/csrc/cf_phase1.h")
 # bytes per k_enum_unrank launch of 2^25 plans (the write counter reads exactly the table bytes)
-ENUM_MEASURED_TRAFFIC = {("b9ac6efd2fcc5a5b", 1 << 25): 7.8191e9}
+ENUM_MEASURED_TRAFFIC = {("4864bdd7d257de68", 1 << 25): 7.8197e9}
 MC_MEASURED_TRAFFIC = {
-    ("7c84b8868934b26b", "c4 phase 2: the 17471 plans phase 1 keeps of 1000000, 1024 sampled requests (seed 0), "
-     "alpha 0.8, then Pareto pruning"): 3.7331e8,
+    ("e108dcd792f1e496", "c4 phase 2: the 17471 plans phase 1 keeps of 1000000, 1024 sampled requests (seed 0), "
+     "alpha 0.8, then Pareto pruning"): 3.7332e8,
 }
 
 
@@ -82,6 +84,22 @@ def kernel_source_id(files=KERNEL_SOURCES):
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
+
+
+def fine_kernel(w, ids):
+    """The simulator that cf_eval_fine launches for these plans of the workload's table."""
+    comps = w.cfg["model"]["components"]
+    gated = [c for c in comps if c.get("gate")]
+    if gated:
+        llms = sum(c["kind"] == "LLM" for c in comps)
+        return "k_fine_gate" if len(gated) == 1 and llms == 2 else "k_fine<true>"
+    # a node's stage instances: its components times its executors of both configurations
+    tab, stages = w.tab, 0
+    for p in ids:
+        stages = max(stages, sum(bin(int(tab.node_comp[v, p])).count("1")
+                                 * (int(tab.node_rep[v, p]) + int(tab.node_rep2[v, p]))
+                                 for v in range(int(tab.n_nodes[p]))))
+    return "k_fine_reg" if stages <= 64 else "k_fine<false>"
 
 
 def _oracle_triples(cfg, seeds, n_req, triples, budget_s):
@@ -493,15 +511,14 @@ def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=-1,
-                    help="timed steps (default: 1 for the whole c4 workload, whose step is one seed of the fine "
-                         "stage, ~40 s; else 2)")
+                    help="timed steps (default: 2, for the whole c4 workload ~16 s each)")
     ap.add_argument("--warmup", type=int, default=1)
     ap.add_argument("--config", default="c4")
     ap.add_argument("--slices", type=int, default=-1, metavar="F",
                     help="each step simulates one slice of the fine stage: every F-th selected plan (all "
-                         "grid rates) on one seed, step g taking plan slice g %% F of seed g // F (default: 1 "
-                         "for the whole c4 workload, i.e. every selected plan on one seed per step, else none: "
-                         "every plan on every seed per step)")
+                         "grid rates) on one seed, step g taking plan slice g %% F of seed g // F (default: 2 "
+                         "for the whole c4 workload, i.e. every other selected plan on one seed per step, else "
+                         "none: every plan on every seed per step)")
     ap.add_argument("--seeds", type=int, default=0, metavar="N",
                     help="simulate only the first N seeds of the workload (a sample of a workload "
                          "too large to run whole; stated in the output)")
@@ -590,11 +607,13 @@ def main():
         w.top_k = min(w.top_k, args.plans)
     F = args.slices
     if F < 0:
-        # c4 whole: one seed per step.  A launch of one seed's 32,000 triples keeps ~8 triples in turn on
-        # each resident wavefront; thinner slices end on their longest triple (~17 s) while the rest idle
-        F = 1 if (args.config == "c4" and args.seeds == 0 and args.plans == 0 and not args.bisect) else 0
+        # c4 whole: half of a seed's triples per step, so that a run of 20 steps and 5 warmup steps ends
+        # within ten minutes.  A launch ends on its longest triples while the other wavefronts idle: one
+        # seed (32,000 triples) 29.5 s and 2.23e10 request-events/s, half of them 15.7 s and 2.10e10, a
+        # quarter 12.0 s and 1.37e10
+        F = 2 if (args.config == "c4" and args.seeds == 0 and args.plans == 0 and not args.bisect) else 0
     if args.steps < 0:
-        args.steps = 1 if F > 0 else 2
+        args.steps = 2
     S = len(w.seeds)
 
     def set_slice(g):
@@ -692,7 +711,7 @@ def main():
                      # the same kernel's VALU lane rate by the counters (instructions x active
                      # lanes / time) as a fraction of the same peak, for this source and workload
                      "counter_valu_lane_frac": MEASURED_LANE_FRAC.get((kernel_source_id(), workload)),
-                     "kernel": "k_fine", "ops_per_event": OPS_PER_EVENT,
+                     "kernel": fine_kernel(w, out["fine_ids"].cpu().numpy()), "ops_per_event": OPS_PER_EVENT,
                      "kernel_ms": sum(fine_ms) / len(fine_ms)},
     }
     if not args.no_cpu_baseline:
