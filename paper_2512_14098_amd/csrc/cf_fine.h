@@ -157,7 +157,17 @@ __device__ __forceinline__ GPtr<T> gptr_at(char *base, size_t off) {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// element i of a trace array's part from element off on (wave-uniform: the
+// element o of a trace array, which may hold any number of seeds.  An arrival in
+// k_fine and the 64 of k_fine_gate's blocks form their nine addresses per lane from
+// one element number: with a base per array in scalar registers (below) more
+// registers spill there: 28 triples of 3,000 requests in k_fine_gate 516 -> 528 ms, in
+// k_fine<true> 608 -> 614 ms; 24,576 triples of 1,000 in k_fine<false> 69.7 -> 70.3 ms.
+template <typename T>
+__device__ __forceinline__ T gload(const T *p, size_t o) {
+  return *(const CF_GLOBAL T *)(p + o);
+}
+
+// k_fine_reg: element i of a trace array's part from element off on (wave-uniform: the
 // seed's first request).  The part's address is formed in 64 bits, because the
 // array may hold any number of seeds; i is a request of one seed, at most 2^26
 // elements of 8 bytes, so that its offset fits 32 bits.
@@ -165,7 +175,7 @@ template <typename T>
 __device__ __forceinline__ T gload(const T *p, size_t off, uint32_t i) {
   const CF_GLOBAL char *part = (const CF_GLOBAL char *)(p + off);
   // kept in scalar registers: without this the compiler adds offsets per lane
-  // (24 triples of 1,000 requests 7.95 ms, with it 7.77)
+  // (24 triples of 1,000 requests 7.95 ms, with it 7.77; 7.90 by element numbers)
   asm("" : "+s"(part));
   return *(const CF_GLOBAL T *)(part + i * (uint32_t)sizeof(T));
 }

@@ -224,16 +224,6 @@ __device__ __forceinline__ void slot_put(const SlotPtr &rr, uint32_t j, const Sl
   const u32x4 v = {w.r, w.k, w.g, w.q};
   *(CF_GLOBAL u32x4 *)((CF_GLOBAL char *)rr.p + (j << 4)) = v;
 }
-// element o of a trace array (any number of seeds).  An arrival forms its nine
-// addresses in 64 bits from one element number: a base per array and a 32-bit
-// offset, as in the simulators in registers, is 1 % slower here (k_fine<true>, 28
-// triples of 3,000 requests, 608 -> 614 ms; k_fine<false>, 24,576 triples of 1,000,
-// 69.7 -> 70.3 ms).
-template <typename T>
-__device__ __forceinline__ T gload(const T *p, size_t o) {
-  return *(const CF_GLOBAL T *)(p + o);
-}
-
 struct Sim {
   const FineArgs *A;
   WaveShared *sh;

@@ -237,15 +237,15 @@ __device__ __forceinline__ void load_arrivals(Gate &S, uint32_t base) {
   S.a_ex = ~0ull;
   S.a_type = CF_MAX_TYPES;
   if (r < (uint32_t)A.n) {
-    const size_t o = (size_t)S.seed * (size_t)A.n;
+    const size_t o = (size_t)S.seed * (size_t)A.n + r;
     const uint64_t tk = S.ticks[r];
-    const uint32_t t = gload(A.type, o, r), ak = gload(A.akey, o, r);
-    const uint64_t k0 = gload(A.rkey0, o, r), k1 = gload(A.rkey1, o, r);
+    const uint32_t t = gload(A.type, o), ak = gload(A.akey, o);
+    const uint64_t k0 = gload(A.rkey0, o), k1 = gload(A.rkey1, o);
     u32x4 w;
-    w.x = (uint32_t)gload(A.prompt, o, r) | ((uint32_t)gload(A.out, o, r) << 16);
-    w.y = gload(A.patches, o, r);
-    w.z = gload(A.aud_in, o, r);
-    w.w = gload(A.aud_out, o, r);
+    w.x = (uint32_t)gload(A.prompt, o) | ((uint32_t)gload(A.out, o) << 16);
+    w.y = gload(A.patches, o);
+    w.z = gload(A.aud_in, o);
+    w.w = gload(A.aud_out, o);
     S.a_t = ((double)tk * 0x1p-32) / S.lam;
     if (t < (uint32_t)m.nt) {
       int alt = 0;
@@ -1135,7 +1135,7 @@ __device__ __forceinline__ void setup_model(Gate &S) {
   }
 }
 
-// 96 VGPRs, 5 wavefronts per SIMD (18 VGPRs and 204 SGPRs spilled): 495 ms on the
+// 96 VGPRs, 5 wavefronts per SIMD (16 VGPRs and 198 SGPRs spilled): 495 ms on the
 // launch of 32,000 triples above; 4 (128 VGPRs) 563 ms, 6 (63 VGPRs spilled) 586 ms.
 __global__ void __launch_bounds__(64, 5) k_fine_gate(const FineArgs *__restrict__ Ap) {
   __shared__ GateLds sh;
