@@ -54,18 +54,18 @@ _W_C4_STEP = ("c4: Full coarse-to-fine sweep of the omni graph on 64 simulated G
               "phase 3 of every 2-th selected plan at every rate on one seed (plan slice g mod 2 of seed g div 2 "
               "at step g), their goodput reduction")
 MEASURED_TRAFFIC = {
-    ("e4d12b7eed477dcc", _W_C4_STEP): 2.4697e13,
-    ("e4d12b7eed477dcc", _W_C1): 9.3816e11,
-    ("e4d12b7eed477dcc", _W_C2_SEEDS2): 2.2424e12,
-    ("e4d12b7eed477dcc", _W_C3_SEED0): 2.1163e12,
+    ("602a175220cd4377", _W_C4_STEP): 2.4690e13,
+    ("602a175220cd4377", _W_C1): 9.3980e11,
+    ("602a175220cd4377", _W_C2_SEEDS2): 2.2394e12,
+    ("602a175220cd4377", _W_C3_SEED0): 2.1158e12,
 }
 # VALU lane rate of the simulation launch by rocprofv3 counters (SQ_INSTS_VALU x SQ_THREAD_CYCLES_VALU /
 # SQ_ACTIVE_INST_VALU / kernel time / PEAK_LANE_OPS), keyed like MEASURED_TRAFFIC
 MEASURED_LANE_FRAC = {
-    ("e4d12b7eed477dcc", _W_C4_STEP): 0.2856,
-    ("e4d12b7eed477dcc", _W_C1): 0.2817,
-    ("e4d12b7eed477dcc", _W_C2_SEEDS2): 0.3561,
-    ("e4d12b7eed477dcc", _W_C3_SEED0): 0.2689,
+    ("602a175220cd4377", _W_C4_STEP): 0.2739,
+    ("602a175220cd4377", _W_C1): 0.2819,
+    ("602a175220cd4377", _W_C2_SEEDS2): 0.3618,
+    ("602a175220cd4377", _W_C3_SEED0): 0.2696,
 }
 ENUM_KERNEL_SOURCES = ("paper_2512_14098_amd/csrc/k_enum.hip", "paper_2512_14098_amd/csrc/cf_internal.h",
                        "paper_2512_14098_amd/csrc/cf_phase1.h")
@@ -609,8 +609,8 @@ def main():
     if F < 0:
         # c4 whole: half of a seed's triples per step, so that a run of 20 steps and 5 warmup steps ends
         # within ten minutes.  A launch ends on its longest triples while the other wavefronts idle: one
-        # seed (32,000 triples) 29.5 s and 2.23e10 request-events/s, half of them 15.7 s and 2.10e10, a
-        # quarter 12.0 s and 1.37e10
+        # seed (32,000 triples) 29.2 s and 2.26e10 request-events/s, half of them 15.4 s and 2.14e10, a
+        # quarter 11.5 s and 1.43e10
         F = 2 if (args.config == "c4" and args.seeds == 0 and args.plans == 0 and not args.bisect) else 0
     if args.steps < 0:
         args.steps = 2
